@@ -29,10 +29,10 @@ struct ProbDesc {
     double *A;             // n x n complex128 working copy (lower triangle used)
     double *Y;             // n x n complex128 reflectors (column c: rows c+1.., Y[c+1,c] = 1)
     double *tau;           // n complex128
-    double *P;             // n x 2NB complex128: [V | W] of the current panel; the exchange slots of the resident form
+    double *P;             // n x 2NB complex128: [V | W] of the current panel
     double *Q;             // n x 2NB complex128: [W | V]
     double *part;          // hemv partial sums: (2*ntile) x n complex128
-    double *tri;           // 5 n^2 doubles: inverse-iteration LU factors, interleaved
+    double *tri;           // 5 n^2 doubles: inverse-iteration LU factors, interleaved; before them the exchange slots of the resident form
     double *Zt;            // n x n: inverse-iteration vectors, entry i of vector k at [i*n + k]
     double *d;             // n   (tridiagonal diagonal)
     double *e;             // n   (off-diagonal, e[n-1] unused)

@@ -115,6 +115,7 @@ int stage1_solve(const Stage1Batch &B, hipStream_t st);
 // every launch.  Chosen for the binary64 variant of those orders; the FP32
 // variant and larger orders take the per-column launches above.
 constexpr int kTrdTeamMax = 2048;
+constexpr int kTrdSoloMax = 128;   // one work-group holds the matrix: nothing is exchanged
 constexpr int kTrdClasses = 6;
 struct Stage1Mixed {
     KernelTimer *timer;        // may be null

@@ -43,7 +43,7 @@ struct ProbDesc {
     double *X;             // NB x n complex128 scratch
     double *X2;            // NB x n complex128 scratch
     int *flag;             // bit 0: NaN/Inf seen in the input, bit 1: the resident tridiagonalisation timed out
-    int *cnt;              // 2n finishing counters (column update, W finish), zeroed at ingest
+    int *cnt;              // 2n finishing counters (column update, W finish), zeroed at ingest; resident form: [0] the largest exponent, later the clusters' starts
     double *scr;           // per row chunk: partial norm (dd), panel dot products, w^H v; reflector scale
 };
 

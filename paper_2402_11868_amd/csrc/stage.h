@@ -117,6 +117,11 @@ int stage1_solve(const Stage1Batch &B, hipStream_t st);
 constexpr int kTrdTeamMax = 2048;
 constexpr int kTrdSoloMax = 128;   // one work-group holds the matrix: nothing is exchanged
 constexpr int kTrdClasses = 6;
+// Exponent of a matrix's largest component as it is kept (positive; 0: no
+// nonzero finite entry), and the power of two that brings it below 1.
+constexpr int kTrdExpBias = 4096;
+__device__ inline int trd_exponent(double big) { return big > 0.0 && big < INFINITY ? ilogb(big) + 1 + kTrdExpBias : 0; }
+__device__ inline int trd_scale(int kept) { return kept ? kept - kTrdExpBias : 0; }
 struct Stage1Mixed {
     KernelTimer *timer;        // may be null
     int nprob;

@@ -133,4 +133,23 @@ __device__ __forceinline__ double block_sum(double v, double *red)
     return s;
 }
 
+// 1 / x from the hardware estimate and two Newton steps (about one rounding;
+// a correctly rounded division is three times the latency)
+__device__ __forceinline__ double rcp_newton(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// a / b from r = 1 / b to about half a unit in the last place: the product
+// corrected by its remainder, as accurate as a division.  (For the tau and
+// scale of a Householder reflector the product alone makes the departure from
+// unitarity a quarter larger.)
+__device__ __forceinline__ double quotient(double a, double b, double r)
+{
+    const double q = a * r;
+    return fma(fma(-q, b, a), r, q);
+}
+
 }  // namespace zk

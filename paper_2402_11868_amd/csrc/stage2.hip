@@ -1825,8 +1825,11 @@ template <int L>
 __device__ __forceinline__ mp<L> wave_total(mp<L> v)
 {
     if constexpr (L == 2) {
-        wave_sum_acc2(v.x[0], v.x[1]);
-        fast_two_sum(v.x[0], v.x[1], v.x[0], v.x[1]);
+        double f = 0.0;
+        wave_sum_acc3(v.x[0], v.x[1], f);
+        double h, l;
+        two_sum(v.x[0], v.x[1], h, l);
+        fast_two_sum(h, l + f, v.x[0], v.x[1]);
         return v;
     } else {
         return wave_sum_mp<L>(v);
@@ -1859,6 +1862,12 @@ __device__ __forceinline__ cmp<L> lane_get(const cmp<L> &z, int from)
 // and several dependent memory trips per column (order 301: 0.90 -> 0.31 ms a
 // launch, quad-double order 192 4.5 -> 1.65 ms).  A column's sum is taken by
 // one wave whatever NT is, so the result does not depend on the launch.
+// In double-double the order of the sums decides how far the solve's rounding
+// carries (residual after one solve, upper eigenvalues of the clustered matrix
+// of order 1024, median: 3.1e-31 column by column, 4.3e-31 with every term
+// added onto the whole sum): lanes add up four rows at a time, the lanes'
+// parts are added without error, and the panel's own terms, whose sum is
+// small, are kept apart from the rest: 3.0e-31.
 // PW: the widest panel of the launch's orders (the LDS it takes sets how many
 // one-wave work-groups share a CU).
 template <int L, int NT, int PW>
@@ -1907,19 +1916,23 @@ __global__ void __launch_bounds__(NT) k_s2_ldl_backsolve(Stage2Batch B)
             CAcc<L> a0, a1;
             a0.init(c_zero<L>());
             a1.init(c_zero<L>());
+            cmp<L> t0 = c_zero<L>(), t1 = t0;
             int cnt = 0;
             for (int r = pend + lane; r < n; r += 64) {
                 const cmp<L> x = ld_cmp<L>(M, plane, yc + r);
                 a0.add_mulc(ld_cmp<L>(M, plane, (size_t)(c0 + j) * ldm + r), x);
                 a1.add_mulc(ld_cmp<L>(M, plane, (size_t)(c0 + j2) * ldm + r), x);
-                if ((++cnt & 15) == 0) {
-                    a0.renorm();
-                    a1.renorm();
+                if (L == 2 && (++cnt & 3) == 0) {   // (few terms are rounded at the size of the whole sum)
+                    t0 = c_add(t0, a0.get());
+                    t1 = c_add(t1, a1.get());
+                    a0.init(c_zero<L>());
+                    a1.init(c_zero<L>());
                 }
             }
-            const cmp<L> v0 = a0.get(), v1 = a1.get();
-            const cmp<L> t0 = {wave_total<L>(v0.re), wave_total<L>(v0.im)};
-            const cmp<L> t1 = {wave_total<L>(v1.re), wave_total<L>(v1.im)};
+            t0 = L == 2 ? c_add(t0, a0.get()) : a0.get();
+            t1 = L == 2 ? c_add(t1, a1.get()) : a1.get();
+            t0 = {wave_total<L>(t0.re), wave_total<L>(t0.im)};
+            t1 = {wave_total<L>(t1.re), wave_total<L>(t1.im)};
             if (lane == 0) {
                 s_sum[j] = t0;
                 if (j + 1 < w) s_sum[j + 1] = t1;
@@ -1949,11 +1962,18 @@ __global__ void __launch_bounds__(NT) k_s2_ldl_backsolve(Stage2Batch B)
             }
             const bool ext = slot == w + lane && lane < w;   // this lane holds a partner row's value
             const cmp<L> xv = ext ? ld_cmp<L>(M, plane, yc + part) : c_zero<L>();
+            // double-double: the panel's own contributions are summed apart from y - s, which
+            // holds the far larger sum, at whose size every term would be rounded
+            const cmp<L> base = lane < w ? c_sub(ld_cmp<L>(M, plane, yc + c0 + lane), s_sum[lane]) : c_zero<L>();
             CAcc<L> acc;
-            acc.init(lane < w ? c_sub(ld_cmp<L>(M, plane, yc + c0 + lane), s_sum[lane]) : c_zero<L>());
+            acc.init(L == 2 ? c_zero<L>() : base);
             cmp<L> x = c_zero<L>();
             for (int i = w - 1; i >= 0; i--) {
-                const cmp<L> mine = acc.get();
+                cmp<L> mine = acc.get();
+                if (L == 2) {
+                    acc.init(mine);
+                    mine = c_add(base, mine);
+                }
                 const cmp<L> xi = lane_get<L>(mine, i);
                 if (lane == i) x = xi;
                 if (lane < i && !(((second >> i) & 1ull) && lane == i - 1)) {

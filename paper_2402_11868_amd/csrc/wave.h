@@ -170,4 +170,41 @@ __device__ __forceinline__ void wave_sum_acc2(double &s, double &e)
     e = (e + l) + err;
 }
 
+// (s, e, f), a sum in three parts, over the wave: the first two added without
+// error, so that a double-double sum is rounded once at its end and not at
+// every step
+__device__ __forceinline__ void acc3(double &s, double &e, double &f, double h, double l, double m)
+{
+    double t, err, u, v;
+    two_sum(s, h, t, err);
+    s = t;
+    two_sum(e, l, t, u);
+    two_sum(t, err, e, v);
+    f += m + (u + v);
+}
+template <int CTRL>
+__device__ __forceinline__ void acc3_dpp(double &s, double &e, double &f)
+{
+    acc3(s, e, f, dpp_get<CTRL>(s), dpp_get<CTRL>(e), dpp_get<CTRL>(f));
+}
+__device__ __forceinline__ void wave_sum_acc3(double &s, double &e, double &f)
+{
+    acc3_dpp<0xB1>(s, e, f);
+    acc3_dpp<0x4E>(s, e, f);
+    acc3_dpp<0x141>(s, e, f);
+    acc3_dpp<0x140>(s, e, f);
+    double h = s, l = e, m = f;
+    lane_swap16(s, h);
+    lane_swap16(e, l);
+    lane_swap16(f, m);
+    acc3(s, e, f, h, l, m);
+    h = s;
+    l = e;
+    m = f;
+    lane_swap32(s, h);
+    lane_swap32(e, l);
+    lane_swap32(f, m);
+    acc3(s, e, f, h, l, m);
+}
+
 }  // namespace zk

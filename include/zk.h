@@ -167,6 +167,15 @@ int zk_ctx_memory(const zk_ctx *ctx, size_t *held, size_t *budget, size_t *high_
  * may be NULL.  ZK_EINVAL for a NULL ctx. */
 int zk_ctx_last_stats(const zk_ctx *ctx, int *iters_hist16, int *rounds, long long *solves);
 
+/* Resident tridiagonalisation since the context was created: *matrices =
+ * matrices (orders 129 .. 2048) whose work-groups exchanged columns, *gave_up
+ * = those of them whose work-groups did not come to run together within the
+ * wait bound (1 s; the environment variable ZK_TRD_WAIT_US at the context's
+ * creation sets another one, 0 gives up at the first wait) and which the
+ * per-column launches reduced instead.  Either pointer may be NULL.
+ * ZK_EINVAL for a NULL ctx. */
+int zk_ctx_team_stats(const zk_ctx *ctx, long long *matrices, long long *gave_up);
+
 /*
  * zk_heev_dd / zk_heev_qd: eigendecompose `count` independent Hermitian
  * matrices A[0..count-1] (sizes may differ) to double-double (out[i].limbs ==

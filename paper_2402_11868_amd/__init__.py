@@ -69,7 +69,7 @@ KERNEL_CLASSES = ["lu_update", "lu_panel", "lu_trsm", "backsolve", "rq", "gs", "
 EXPORTED = ["zk_prof_enable", "zk_prof_classes", "zk_prof_reset", "zk_prof_read", "zk_opts_default", "zk_ctx_create", "zk_ctx_destroy", "zk_status_str", "zk_ctx_last_error",
             "zk_workspace_bytes", "zk_heev_dd", "zk_heev_qd", "zk_heev_dd_allpairs", "zk_svd_dd", "zk_mps_two_site_dd", "zk_heev_fp64", "zk_rqi_refine",
             "zk_session_create", "zk_session_submit", "zk_session_poll", "zk_session_times", "zk_session_destroy",
-            "zk_ctx_memory", "zk_ctx_last_stats", "zk_heev_dd_noalloc", "zk_heev_mp",
+            "zk_ctx_memory", "zk_ctx_last_stats", "zk_ctx_team_stats", "zk_heev_dd_noalloc", "zk_heev_mp",
             "zk_mps_create", "zk_mps_destroy", "zk_mps_apply1", "zk_mps_apply2", "zk_mps_bond", "zk_mps_site",
             "zk_mps_latencies"]
 
@@ -111,6 +111,7 @@ def load(path: str = LIB_PATH):
                                        ctypes.POINTER(I), ctypes.POINTER(ZkOpts)]
     lib.zk_heev_fp64.argtypes = [P, I, ctypes.POINTER(ZkHerm), ctypes.POINTER(P), ctypes.POINTER(P), ctypes.POINTER(I)]
     lib.zk_rqi_refine.argtypes = [P, I, ctypes.POINTER(ZkHerm), I, P, P, I, ctypes.POINTER(ZkEigOut), ctypes.POINTER(ZkOpts)]
+    lib.zk_ctx_team_stats.argtypes = [P, ctypes.POINTER(ctypes.c_longlong), ctypes.POINTER(ctypes.c_longlong)]
     lib.zk_ctx_last_stats.argtypes = [P, ctypes.POINTER(I), ctypes.POINTER(I), ctypes.POINTER(ctypes.c_longlong)]
     SZ = ctypes.POINTER(ctypes.c_size_t)
     lib.zk_ctx_memory.argtypes = [P, SZ, SZ, SZ, SZ]
@@ -203,6 +204,13 @@ class Context:
         solves = ctypes.c_longlong()
         load().zk_ctx_last_stats(self.handle, hist, ctypes.byref(rounds), ctypes.byref(solves))
         return {"iters_hist": list(hist), "rounds": rounds.value, "solves": solves.value}
+
+    def team_stats(self) -> dict:
+        """Matrices of the resident tridiagonalisation that exchanged columns,
+        and those that gave up waiting (zk_ctx_team_stats)."""
+        m, g = ctypes.c_longlong(), ctypes.c_longlong()
+        load().zk_ctx_team_stats(self.handle, ctypes.byref(m), ctypes.byref(g))
+        return {"matrices": m.value, "gave_up": g.value}
 
     def close(self):
         # sessions run on this context: stop them first

@@ -62,6 +62,7 @@ extern "C" int zk_ctx_create(int device, void *hip_stream, size_t hbm_budget, zk
     zk_ctx *c = new zk_ctx();
     c->device = device;
     c->budget = hbm_budget ? hbm_budget : ((size_t)64 << 30);
+    if (const char *us = std::getenv("ZK_TRD_WAIT_US")) c->trd_wait = 100ull * std::strtoull(us, nullptr, 10);
     if (hip_stream) {
         c->stream = (hipStream_t)hip_stream;
         c->own_stream = false;
@@ -622,6 +623,7 @@ static int run_stage1_resident(zk_ctx *ctx, std::vector<int> set, const zk_herm 
         S1.dev_largest = (int *)(d_wgs + wgs.size());
         S1.host_largest = ctx->pin;
         S1.largest_read = ctx->ev_pin;
+        S1.wait = ctx->trd_wait;
         int *d_fl = (int *)(d_wgs + wgs.size() + 1);
         wgs.push_back(make_int2(0, 0));   // dev_largest
         std::vector<char> table(align_up(sizeof(ProbDesc) * np) + sizeof(int2) * wgs.size());
@@ -671,8 +673,11 @@ int run_stage1(zk_ctx *ctx, int count, const zk_herm *A, const std::vector<doubl
     if ((rc = columns(cols, fp32)) != ZK_OK) return rc;
     // a team that never ran as a whole (its compute units held by other waiting kernels): per-column launches
     std::vector<int> late;
-    for (int i : team)
+    for (int i : team) {
+        if (A[i].n > kTrdSoloMax) ctx->team_mats++;
         if (fl[i] & 2) late.push_back(i);
+    }
+    ctx->team_late += (long long)late.size();
     if ((rc = columns(late, std::vector<int>())) != ZK_OK) return rc;
     // non-finite input?
     for (int i = 0; i < count; i++)
@@ -1150,6 +1155,14 @@ extern "C" int zk_heev_qd(zk_ctx *ctx, int count, const zk_herm *A, zk_eig_out *
     if (ctx) ctx->last = Stage2Stats();
     if (opts && opts->refine != 0) return ctx ? ctx->fail(ZK_EINVAL, "the all-pairs refinement gives double-double output only") : ZK_EINVAL;
     return settle(ctx, run_heev<4>(ctx, count, A, out, opts, ctx ? &ctx->last : nullptr));
+}
+
+extern "C" int zk_ctx_team_stats(const zk_ctx *ctx, long long *matrices, long long *gave_up)
+{
+    if (!ctx) return ZK_EINVAL;
+    if (matrices) *matrices = ctx->team_mats;
+    if (gave_up) *gave_up = ctx->team_late;
+    return ZK_OK;
 }
 
 extern "C" int zk_ctx_last_stats(const zk_ctx *ctx, int *iters_hist16, int *rounds, long long *solves)

@@ -117,6 +117,7 @@ int stage1_solve(const Stage1Batch &B, hipStream_t st);
 constexpr int kTrdTeamMax = 2048;
 constexpr int kTrdSoloMax = 128;   // one work-group holds the matrix: nothing is exchanged
 constexpr int kTrdClasses = 6;
+constexpr unsigned long long kTrdWait = 100000000ull;   // 1 s of the 100 MHz wall clock: bound of a work-group's wait for its team
 // Exponent of a matrix's largest component as it is kept (positive; 0: no
 // nonzero finite entry), and the power of two that brings it below 1.
 constexpr int kTrdExpBias = 4096;
@@ -133,12 +134,13 @@ struct Stage1Mixed {
     int *dev_largest;          // device, zero: the largest cluster's length
     int *host_largest;         // page-locked host copy
     hipEvent_t largest_read;   // recorded when the copy is done
+    unsigned long long wait;   // bound of a work-group's wait (wall clock ticks)
     double tri_gap_rel;
 };
 int trd_team_class(int n);
 int trd_team_size(int n);
 void trd_team_table(const int *orders, int np, int cls, std::vector<int2> &out);
-int trd_team_run(int cls, ProbDesc *dev_probs, const int2 *dev_wgs, int count, hipStream_t st);
+int trd_team_run(int cls, ProbDesc *dev_probs, const int2 *dev_wgs, int count, unsigned long long limit, hipStream_t st);
 int backt_cols_run(int cls, ProbDesc *dev_probs, int np, int max_n, hipStream_t st);
 int stage1_mixed_run(const Stage1Mixed &B, hipStream_t st);
 

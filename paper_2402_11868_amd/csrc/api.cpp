@@ -74,7 +74,11 @@ extern "C" int zk_ctx_create(int device, void *hip_stream, size_t hbm_budget, zk
         c->own_stream = true;
     }
     if (hipHostMalloc((void **)&c->pin, 64, hipHostMallocDefault) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev_pin, hipEventDisableTiming) != hipSuccess) {
+        hipEventCreateWithFlags(&c->ev_pin, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_teams, hipEventDisableTiming) != hipSuccess ||
+        hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
+        if (c->ev_teams) hipEventDestroy(c->ev_teams);
+        if (c->ev_pin) hipEventDestroy(c->ev_pin);
         if (c->pin) hipHostFree(c->pin);
         if (c->own_stream) hipStreamDestroy(c->stream);
         delete c;
@@ -98,6 +102,12 @@ extern "C" int zk_ctx_destroy(zk_ctx *ctx)
         }
     for (hipEvent_t &e : ctx->ev)
         if (e) hipEventDestroy(e);
+    {
+        TeamGate &gate = team_gate(ctx->device);
+        std::lock_guard<std::mutex> lk(gate.mu);
+        if (gate.last == ctx->ev_teams) gate.last = nullptr;   // (its stream was waited for above)
+    }
+    hipEventDestroy(ctx->ev_teams);
     hipEventDestroy(ctx->ev_pin);
     hipHostFree(ctx->pin);
     if (ctx->own_stream) hipStreamDestroy(ctx->stream);
@@ -624,6 +634,8 @@ static int run_stage1_resident(zk_ctx *ctx, std::vector<int> set, const zk_herm 
         S1.host_largest = ctx->pin;
         S1.largest_read = ctx->ev_pin;
         S1.wait = ctx->trd_wait;
+        S1.device = ctx->device;
+        S1.teams_done = ctx->ev_teams;
         int *d_fl = (int *)(d_wgs + wgs.size() + 1);
         wgs.push_back(make_int2(0, 0));   // dev_largest
         std::vector<char> table(align_up(sizeof(ProbDesc) * np) + sizeof(int2) * wgs.size());
@@ -659,7 +671,8 @@ int run_stage1(zk_ctx *ctx, int count, const zk_herm *A, const std::vector<doubl
     int rc;
     std::vector<int> team, cols, fl(count, 0);
     for (int i = 0; i < count; i++)
-        (A[i].n >= 2 && A[i].n <= kTrdTeamMax && (fp32.empty() || !fp32[i]) ? team : cols).push_back(i);
+        (A[i].n >= 2 && A[i].n <= kTrdTeamMax && trd_team_size(A[i].n) <= ctx->cus && (fp32.empty() || !fp32[i]) ? team : cols)
+            .push_back(i);
     if (!team.empty() && (rc = run_stage1_resident(ctx, team, A, hf, w0, V0, flag, fl)) != ZK_OK) return rc;
     auto columns = [&](const std::vector<int> &set, const std::vector<int> &f32) -> int {
         if (set.empty()) return ZK_OK;

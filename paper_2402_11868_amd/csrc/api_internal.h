@@ -111,6 +111,8 @@ struct zk_ctx {
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     int *pin = nullptr;                // page-locked host words for small read-backs
     hipEvent_t ev_pin = nullptr;       // recorded after such a read-back
+    hipEvent_t ev_teams = nullptr;     // recorded behind its launches with teams (TeamGate)
+    int cus = 0;                       // compute units of the device
     unsigned long long trd_wait = zk::kTrdWait;       // bound of the resident tridiagonalisation's waits
     long long team_mats = 0, team_late = 0;           // matrices it was launched for, and those that gave up
     Stage2Stats last;        // counters of the last zk_heev_dd / zk_heev_qd call

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cstddef>
+#include <mutex>
 #include <vector>
 
 #include "common.h"
@@ -123,7 +124,19 @@ constexpr unsigned long long kTrdWait = 100000000ull;   // 1 s of the 100 MHz wa
 constexpr int kTrdExpBias = 4096;
 __device__ inline int trd_exponent(double big) { return big > 0.0 && big < INFINITY ? ilogb(big) + 1 + kTrdExpBias : 0; }
 __device__ inline int trd_scale(int kept) { return kept ? kept - kTrdExpBias : 0; }
+// Teams of two contexts on one device could each hold some of the compute
+// units the other waits for.  So the launches with teams (orders above
+// kTrdSoloMax) of a device run one after another, whatever the streams: each
+// waits for the event of the one before.  Held from that wait to the record of
+// the own event; the host never waits for the device in between.
+struct TeamGate {
+    std::mutex mu;
+    hipEvent_t last = nullptr;   // recorded behind the latest launches with teams (an event of their context)
+};
+TeamGate &team_gate(int device);
 struct Stage1Mixed {
+    int device;
+    hipEvent_t teams_done;     // the context's event behind its launches with teams
     KernelTimer *timer;        // may be null
     int nprob;
     const int *orders;         // host, nprob entries

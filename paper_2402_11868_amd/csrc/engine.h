@@ -99,7 +99,7 @@ class Stage2Engine {
     ~Stage2Engine()
     {
         // enqueued copies may still read the lists below (a call that failed half-way)
-        if (gs_pending || rr_pending || solve_pending) hipStreamSynchronize(st);
+        if (up_pending || rq_pending || gs_pending || rr_pending || solve_pending) sync();
         for (S2Prob *p : live) release(p);
         if (gsbuf) {
             ctx->dev_free(gsbuf);
@@ -391,7 +391,7 @@ class Stage2Engine {
             for (const CopySpan &c : sp)
                 HIPCHK_(gather ? hipMemcpyAsync(host.data() + c.off, c.p, 8 * (size_t)c.count, hipMemcpyDeviceToHost, st)
                                : hipMemcpyAsync(c.p, host.data() + c.off, 8 * (size_t)c.count, hipMemcpyHostToDevice, st));
-            HIPCHK_(hipStreamSynchronize(st));
+            HIPCHK_(sync());
             return ZK_OK;
         }
         CopySpan *d = (CopySpan *)ctx->s2vec.p;
@@ -400,7 +400,7 @@ class Stage2Engine {
         if (!gather) HIPCHK_(hipMemcpyAsync(buf, host.data(), 8 * total, hipMemcpyHostToDevice, st));
         if (copy_spans(d, (int)sp.size(), largest, buf, gather, st)) return ctx->fail(ZK_EDEVICE, "copy launch failed");
         if (gather) HIPCHK_(hipMemcpyAsync(host.data(), buf, 8 * total, hipMemcpyDeviceToHost, st));
-        HIPCHK_(hipStreamSynchronize(st));
+        HIPCHK_(sync());
         return ZK_OK;
     }
 
@@ -486,6 +486,7 @@ class Stage2Engine {
         d_gcls = (GsCluster *)mb;
         mb += s2_align(sizeof(GsCluster) * total_pairs);
         d_gscratch = (double *)mb;
+        if (up_pending) HIPCHK_(sync());
         hp.resize(total_pairs);
         hprobs.resize(np);
         for (size_t i = 0; i < np; i++) {
@@ -495,9 +496,9 @@ class Stage2Engine {
                 hp[base[i] + k].prob = (int)i;
             }
         }
+        up_pending = true;   // the copies may still read hp and hprobs after this returns
         HIPCHK_(hipMemcpyAsync(d_pairs, hp.data(), sizeof(PairDesc) * total_pairs, hipMemcpyHostToDevice, st));
         HIPCHK_(hipMemcpyAsync(d_probs, hprobs.data(), sizeof(RqiProb) * np, hipMemcpyHostToDevice, st));
-        // (hp and hprobs stay as they are until the download that ends the round)
         up = set;
         return ZK_OK;
     }
@@ -505,7 +506,7 @@ class Stage2Engine {
     int download(const std::vector<S2Prob *> &set)
     {
         HIPCHK_(hipMemcpyAsync(hp.data(), d_pairs, sizeof(PairDesc) * total_pairs, hipMemcpyDeviceToHost, st));
-        HIPCHK_(hipStreamSynchronize(st));
+        HIPCHK_(sync());
         for (size_t i = 0; i < set.size(); i++)
             for (int k = 0; k < set[i]->npairs; k++) set[i]->pairs[k] = hp[base[i] + k];
         return ZK_OK;
@@ -514,7 +515,9 @@ class Stage2Engine {
     int run_rq(const std::vector<int> &idx, int final_pass)
     {
         if (idx.empty()) return ZK_OK;
-        rq_list = idx;   // the copy may still read it after this returns
+        if (rq_pending) HIPCHK_(sync());
+        rq_list = idx;
+        rq_pending = true;   // the copy may still read it after this returns
         HIPCHK_(hipMemcpyAsync(d_active, rq_list.data(), 4 * rq_list.size(), hipMemcpyHostToDevice, st));
         Stage2Batch B = batch_base();
         B.count = (int)idx.size();
@@ -532,8 +535,7 @@ class Stage2Engine {
     {
         std::vector<GsCluster> &cls = gs_cls;   // (members: the copies may still read them after this returns)
         std::vector<int> &list = gs_list;
-        if (gs_pending) HIPCHK_(hipStreamSynchronize(st));
-        gs_pending = false;
+        if (gs_pending) HIPCHK_(sync());
         cls.clear();
         list.clear();
         GsPlan G;
@@ -627,7 +629,7 @@ class Stage2Engine {
             const int id = tm ? tm->begin(KC_REORTH, lw_cols, st) : -1;
             if (dd_lowdin(lw, 2, gsbuf, st)) return ctx->fail(ZK_EDEVICE, "re-orthogonalisation launch failed");
             if (tm) tm->end(id, st);
-            HIPCHK_(hipStreamSynchronize(st));
+            HIPCHK_(sync());
         }
         if (cls.empty()) return ZK_OK;
         // plan storage sized from the plan itself: clusters, column lists,
@@ -642,6 +644,7 @@ class Stage2Engine {
         GsCluster *g_cls = (GsCluster *)gsbuf;
         int *g_list = (int *)((char *)gsbuf + b_cls);
         double *g_scr = (double *)((char *)gsbuf + b_cls + b_list);
+        gs_pending = true;
         HIPCHK_(hipMemcpyAsync(g_cls, cls.data(), sizeof(GsCluster) * cls.size(), hipMemcpyHostToDevice, st));
         HIPCHK_(hipMemcpyAsync(g_list, list.data(), 4 * list.size(), hipMemcpyHostToDevice, st));
         G.ncl = (int)cls.size();
@@ -654,7 +657,6 @@ class Stage2Engine {
         const int id = tm ? tm->begin(global ? KC_REORTH : KC_GS, (double)list.size(), st) : -1;
         if (stage2_gs<L>(G, d_probs, global ? nullptr : d_pairs, st)) return ctx->fail(ZK_EDEVICE, "Gram-Schmidt launch failed");
         if (tm) tm->end(id, st);
-        gs_pending = true;
         return ZK_OK;
     }
 
@@ -672,8 +674,7 @@ class Stage2Engine {
         int rc = ensure_slots(max_n, nact);
         if (rc != ZK_OK) return rc;
         std::vector<int> &lst = solve_list, ord;   // (a member: the copy may still read it after this returns)
-        if (solve_pending) HIPCHK_(hipStreamSynchronize(st));
-        solve_pending = false;
+        if (solve_pending) HIPCHK_(sync());
         lst.clear();
         for (auto it = by_n.rbegin(); it != by_n.rend(); ++it)
             for (int g : it->second) {
@@ -705,6 +706,7 @@ class Stage2Engine {
             for (int k = 0; k < 3; k++)
                 if (!ctx->ev[k]) HIPCHK_(hipEventCreateWithFlags(&ctx->ev[k], hipEventDisableTiming));
         }
+        solve_pending = true;
         HIPCHK_(hipMemcpyAsync(d_active, lst.data(), 4 * lst.size(), hipMemcpyHostToDevice, st));
         Stage2Batch B = batch_base();
         B.ldl = ldl ? 1 : 0;
@@ -739,7 +741,6 @@ class Stage2Engine {
             }
             if (stage2_solve<L>(B, ord.data() + c0, st)) return ctx->fail(ZK_EDEVICE, "solve launch failed");
         }
-        solve_pending = true;
         return ZK_OK;
     }
 
@@ -769,12 +770,12 @@ class Stage2Engine {
             const int n = p->rp.n;
             std::vector<double> sig((size_t)L * n);
             HIPCHK_(hipMemcpyAsync(sig.data(), p->rp.sigma, 8 * sig.size(), hipMemcpyDeviceToHost, st));
-            HIPCHK_(hipStreamSynchronize(st));
+            HIPCHK_(sync());
             for (int k = 0; k < p->npairs; k++)
                 if (mark[pi][k])
                     for (int l = 0; l < L; l++) sig[(size_t)l * n + k] = 0.0;
             HIPCHK_(hipMemcpyAsync(p->rp.sigma, sig.data(), 8 * sig.size(), hipMemcpyHostToDevice, st));
-            HIPCHK_(hipStreamSynchronize(st));
+            HIPCHK_(sync());
         }
         int rc = solve_pairs(by_n, cnt, false);
         if (rc != ZK_OK) return rc;
@@ -1006,7 +1007,7 @@ class Stage2Engine {
         PrrDesc *d_desc = (PrrDesc *)buf;
         int rc = ZK_OK;
         auto cleanup = [&]() {
-            hipStreamSynchronize(st);
+            sync();
             ctx->dev_free(buf);
             ctx->extra -= bytes;
         };
@@ -1045,8 +1046,7 @@ class Stage2Engine {
     {
         std::vector<GsCluster> &cls = rr_cls;   // (members: the copies may still read them after this returns)
         std::vector<int> &list = rr_list;
-        if (rr_pending) HIPCHK_(hipStreamSynchronize(st));
-        rr_pending = false;
+        if (rr_pending) HIPCHK_(sync());
         cls.clear();
         list.clear();
         long long sofs = 0;
@@ -1076,6 +1076,7 @@ class Stage2Engine {
         if (rc != ZK_OK) return rc;
         GsCluster *g_cls = (GsCluster *)gsbuf;
         int *g_list = (int *)((char *)gsbuf + b_cls);
+        rr_pending = true;
         HIPCHK_(hipMemcpyAsync(g_cls, cls.data(), sizeof(GsCluster) * cls.size(), hipMemcpyHostToDevice, st));
         HIPCHK_(hipMemcpyAsync(g_list, list.data(), 4 * list.size(), hipMemcpyHostToDevice, st));
         GsPlan G;
@@ -1088,7 +1089,6 @@ class Stage2Engine {
         const int id = tm ? tm->begin(KC_GS, (double)list.size(), st) : -1;
         if (stage2_rr<L>(G, d_probs, L == 2 ? 10 : 14, st)) return ctx->fail(ZK_EDEVICE, "Rayleigh-Ritz launch failed");
         if (tm) tm->end(id, st);
-        rr_pending = true;
         return ZK_OK;
     }
 
@@ -1174,7 +1174,7 @@ class Stage2Engine {
         HIPCHK_(hipMemcpyAsync(d_pairs, sub.data(), sizeof(PairDesc) * sub.size(), hipMemcpyHostToDevice, st));
         HIPCHK_(hipMemcpyAsync(d_dst, subdst.data(), 4 * subdst.size(), hipMemcpyHostToDevice, st));
         if (stage2_output<L>(d_pairs, d_probs, d_dst, (int)sub.size(), st)) return ctx->fail(ZK_EDEVICE, "output launch failed");
-        HIPCHK_(hipStreamSynchronize(st));
+        HIPCHK_(sync());
         std::vector<S2Prob *> keep;
         std::vector<char> isfin(live.size(), 0);
         for (int pi : fin) isfin[pi] = 1;
@@ -1238,7 +1238,14 @@ class Stage2Engine {
 
     std::vector<int> rq_list, gs_list, rr_list, solve_list;   // sources of enqueued uploads
     std::vector<GsCluster> gs_cls, rr_cls;
-    bool gs_pending = false, rr_pending = false, solve_pending = false;
+    // enqueued uploads that may still read their sources: hp and hprobs, the lists above
+    bool up_pending = false, rq_pending = false, gs_pending = false, rr_pending = false, solve_pending = false;
+    hipError_t sync()
+    {
+        const hipError_t e = hipStreamSynchronize(st);
+        up_pending = rq_pending = gs_pending = rr_pending = solve_pending = false;
+        return e;
+    }
     std::vector<PairDesc> hp;
     std::vector<RqiProb> hprobs;
     std::vector<S2Prob *> up;

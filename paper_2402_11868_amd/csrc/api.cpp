@@ -388,7 +388,7 @@ static int run_stage2(zk_ctx *ctx, std::vector<RqiProb> &probs, const std::vecto
         store[i].info = infos[i];
         batch.push_back(&store[i]);
     }
-    Stage2Engine<L> eng(ctx, O, stats, true);
+    Stage2Engine<L> eng(ctx, O, stats);
     int rc = eng.add(batch);
     while (rc == ZK_OK && eng.any_live()) rc = eng.round();
     if (stats) stats->rounds = eng.rounds;

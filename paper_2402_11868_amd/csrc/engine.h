@@ -89,10 +89,7 @@ struct S2Prob {
 template <int L>
 class Stage2Engine {
   public:
-    // one_call: the matrices come in one add() and the call ends with the last
-    // of them (not a session, whose requests leave one by one)
-    Stage2Engine(zk_ctx *c, const ResolvedOpts &o, Stage2Stats *s, bool one_call = false)
-        : ctx(c), O(o), stats(s), one_call_(one_call)
+    Stage2Engine(zk_ctx *c, const ResolvedOpts &o, Stage2Stats *s) : ctx(c), O(o), stats(s)
     {
         st = c->stream;
         // ZK_S2_SPLIT=0: every chunk of pairs in one group (for measurements)
@@ -132,10 +129,9 @@ class Stage2Engine {
     int add_batch(const std::vector<S2Prob *> &batch)
     {
         int rc;
-        // One allocation for the matrices of a call while it takes at most a
-        // sixteenth of the budget: it is kept until the last of them is done.
-        // Else one for each, given back with its matrix; so always in a
-        // session, whose admission counts on that.
+        // One allocation for a batch of several matrices while it takes at
+        // most a sixteenth of the budget (it is kept until the last of them
+        // is done), else one for each.
         size_t all_bytes = 0;
         for (S2Prob *p : batch) {
             const size_t n = (size_t)p->rp.n;
@@ -144,7 +140,7 @@ class Stage2Engine {
         }
         char *next = nullptr;
         std::shared_ptr<VecChunk> chunk;
-        if (one_call_ && batch.size() > 1 && !ctx->arena && all_bytes <= ctx->budget / 16 && ctx->make_room(all_bytes)) {
+        if (batch.size() > 1 && !ctx->arena && all_bytes <= ctx->budget / 16 && ctx->make_room(all_bytes)) {
             void *mem = nullptr;
             const std::string err = ctx->err;   // a refused allocation is not the call's error
             if (ctx->dev_alloc(&mem, all_bytes) == ZK_OK) {
@@ -298,7 +294,6 @@ class Stage2Engine {
     zk_ctx *ctx;
     ResolvedOpts O;
     Stage2Stats *stats;
-    bool one_call_;
     hipStream_t st;
     // device tables of the current upload
     std::vector<int> base;   // pair-table offset of every uploaded matrix

@@ -112,6 +112,18 @@ class Stage2Engine {
 
     bool any_live() const { return !live.empty(); }
 
+    // Bytes of shared iterate storage whose matrices are done; they go back
+    // with the last matrix of their add().
+    size_t retained() const
+    {
+        std::map<const VecChunk *, size_t> used;
+        for (const S2Prob *p : live)
+            if (p->chunk) used[p->chunk.get()] += p->vecbytes;
+        size_t sum = 0;
+        for (const auto &kv : used) sum += kv.first->bytes - kv.second;
+        return sum;
+    }
+
     // Prepare new matrices (clusters, start vectors, Gram-Schmidt, Rayleigh-Ritz,
     // first Rayleigh quotients) and let them join the iteration.  On failure,
     // the iterate storage of every batch member that did not join is given

@@ -6,7 +6,8 @@
 //   admit    at every round boundary the scheduler admits queued requests in
 //            arrival order while the sum of admitted footprints fits the
 //            session budget (a request larger than the whole budget is
-//            refused at submit)
+//            refused at submit); storage that finished requests share with
+//            running ones counts as well
 //   stage 1  newly admitted requests of equal order share the binary64
 //            launches
 //   stage 2  every admitted request's pairs join the same Rayleigh-quotient
@@ -282,7 +283,8 @@ void zk_session::loop()
                 cv_work.wait(lk, [&] { return stop || !queue.empty(); });
             if (stop) break;
             // admission by footprint, in arrival order
-            while (!queue.empty() && (inflight == 0 || inflight + queue.front()->foot <= budget)) {
+            const size_t kept = e2->retained() + e4->retained();
+            while (!queue.empty() && (inflight == 0 || inflight + kept + queue.front()->foot <= budget)) {
                 Request *r = queue.front();
                 queue.pop_front();
                 r->state = RQ_RUNNING;

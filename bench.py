@@ -305,6 +305,28 @@ def mps_leg(Z, ctx, torch, chi=128):
     return out
 
 
+def stage1_leg(Z, ctx, torch, Ad, runs=5):
+    """The binary64 stage alone on the headline matrix: ms per call (median)
+    and the rate at its 16/3 n^3 + 8 n^3 real operations (reduction and
+    back-transformation), the reduction's own time from one instrumented call."""
+    n = Ad.shape[0]
+    ts = []
+    for _ in range(runs + 1):
+        t0 = time.perf_counter()
+        Z.heev_fp64(ctx, [Ad])
+        torch.cuda.synchronize()
+        ts.append(time.perf_counter() - t0)
+    t = sorted(ts[1:])[runs // 2]
+    ctx.prof(True)
+    ctx.prof_reset()
+    Z.heev_fp64(ctx, [Ad])
+    torch.cuda.synchronize()
+    prof = ctx.prof_read()
+    ctx.prof(False)
+    return {"ms_per_call": t * 1e3, "tflops": (16.0 / 3.0 + 8.0) * n**3 / t / 1e12,
+            "reduction_ms": prof["trd_vec"][0], "tridiagonal_ms": prof["tridiag"][0], "backtransform_ms": prof["backt"][0]}
+
+
 def c1_leg(Z, ctx, torch, runs=100, warm=10, tol=1e-30):
     """The 64 x 64 workload (one eigenvalue exactly 2^-20, the rest 2^(-k/2),
     trace 1): median wall time of `runs` zk_heev_dd calls after `warm`
@@ -787,6 +809,8 @@ def main():
         log("batch of 256 x 128^2")
         out["batch"] = batch_leg(Z, ctx, torch)
     if not args.headline_only:
+        log("binary64 stage alone")
+        out["stage1_resident"] = stage1_leg(Z, ctx, torch, Ad)
         log("64 x 64 workload")
         out["c1"] = c1_leg(Z, ctx, torch)
         log("quad-double companions")

@@ -434,7 +434,8 @@ int zk_rqi_refine(zk_ctx *ctx, int limbs_out, const zk_herm *A, int k, const dou
  * X^H R (work: flops), 16 its double-double GEMMs (work: complex
  * double-double multiply-adds), 17 its other kernels.  Classes 8 and 9 belong
  * to the per-column tridiagonalisation (order 1, orders above 2048, the FP32
- * start); the resident form of the other orders is one launch in class 11.
+ * start); the resident form of the other orders is in class 11, one launch for
+ * each register-file class (orders up to 64, 128, 256, 512, 1024, 2048) present.
  * zk_prof_read waits for the recorded events.
  */
 int zk_prof_enable(zk_ctx *ctx, int on);

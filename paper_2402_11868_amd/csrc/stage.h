@@ -231,9 +231,16 @@ __host__ __device__ inline int ldl_wcol(int n) { return n + 2 + kLdlLA; }
 // kernel's Schur-complement sums grow with the width (n nb / 4 of the n^2 / 6
 // multiply-adds of a pair) and run on one work-group; the trailing update
 // spreads over the chip but reads and writes its block once per panel.
-// Measured with 16 / 32 columns: order 301 21.0 / 23.0 ms, SVD 200 x 120 41.5
-// / 43.9 ms, quad-double 2 x 192 118 / 122 ms; order 1024, where the update's
-// traffic counts, 551 / 522 ms.
+// Narrow panels also leave a smaller residual, which saves solves where the
+// tolerance is near the rounding (random matrices).  Measured with 16 / 32
+// columns, ms a call: one random matrix of order 320 17.4 / 19.1, 400 33.3 /
+// 34.5, 512 69.9 / 80.9; one graded one (2^(-39 k / n)) of order 256 9.34 /
+// 9.59, 400 25.4 / 25.3, 512 51.2 / 51.1; 256 of order 128 103 / 109, 8 of
+// order 400 130 / 128, 4 of order 512 154 / 151, 4 of order 640 335 / 324;
+// clustered, order 448 38.9 / 37.5, 640 120.6 / 119.3, 1024 551 / 522.
+// Quad-double, order 192 61 / 70, 384 333 / 344, 512 825 / 838.
+// (Above 512 random matrices would gain still, 640 161 / 250, and the others
+// lose up to 5 per cent.)
 __host__ __device__ constexpr int ldl_nb(int L, int n) { return L == 4 || n <= 512 ? 16 : 32; }
 struct LuSlot {
     double *M;      // 2L planes of ldm x (n+6+kLuNB) doubles

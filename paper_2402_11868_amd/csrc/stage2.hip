@@ -2197,8 +2197,6 @@ __global__ void __launch_bounds__(256) k_gs_update(const GsCluster *cls, const i
     st_cmp<L>(P.vec, nn, (size_t)cj * n + r, acc.get());
 }
 
-// inside the block: modified Gram-Schmidt (twice) and normalisation; the
-// coefficients of a member are computed by the four waves in parallel
 // Gram matrix of the block, one row slice per blockIdx.x; the tiles ta <= tc
 // of kGsT x kGsT (blockIdx.y); entry (a, c) = v_a^H v_c.
 constexpr int kGramTiles = RB / kGsT * (RB / kGsT + 1) / 2;

@@ -132,7 +132,9 @@ void zk_opts_default(zk_opts *o);
 
 /* Create a context on HIP device `device`.  hip_stream: a hipStream_t of the
  * caller (e.g. torch.cuda.current_stream().cuda_stream) or NULL for a private
- * stream.  hbm_budget: maximum workspace bytes the library may hold (0 = 64 GiB).
+ * stream.  The library's work is ordered by that stream alone: with a private
+ * stream, inputs and outputs have to be free of pending work when an entry
+ * point is called.  hbm_budget: maximum workspace bytes the library may hold (0 = 64 GiB).
  * Returns ZK_OK and *out, or ZK_EINVAL / ZK_EDEVICE. */
 int zk_ctx_create(int device, void *hip_stream, size_t hbm_budget, zk_ctx **out);
 

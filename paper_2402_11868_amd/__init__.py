@@ -167,6 +167,15 @@ class Context:
         self.handle = h
         self._sessions = []
 
+    def _inputs_ready(self):
+        """Inputs, their column-major copies and the cleared outputs are written
+        on torch's current stream.  Unless that is the stream the context works
+        on (the default stream never is: the context then has a private one),
+        nothing orders the library's work behind it, so wait for it."""
+        cur = torch.cuda.current_stream(self.device)
+        if cur.cuda_stream == 0 or cur.cuda_stream != self.stream.cuda_stream:
+            cur.synchronize()
+
     def prof(self, on: bool = True):
         load().zk_prof_enable(self.handle, int(bool(on)))
 
@@ -303,6 +312,7 @@ def heev(ctx: Context, mats, limbs_out: int = 2, opts: ZkOpts | None = None, sta
         outs.append((w, V, info, H[i].n))
     op = ctypes.byref(opts) if opts is not None else None
     f = (lib.zk_heev_dd_noalloc if noalloc else lib.zk_heev_dd) if limbs_out == 2 else lib.zk_heev_qd
+    ctx._inputs_ready()
     rc = f(ctx.handle, count, H, O, op)
     if stats is not None:
         stats.update(ctx.last_stats())
@@ -328,6 +338,7 @@ def heev_allpairs(ctx: Context, mats, opts: ZkOpts | None = None):
         O[i] = o
         outs.append((w, V, info, H[i].n))
     op = ctypes.byref(opts) if opts is not None else None
+    ctx._inputs_ready()
     rc = lib.zk_heev_dd_allpairs(ctx.handle, count, H, O, op)
     if rc not in (ZK_OK, ZK_ENOCONV):
         raise RuntimeError(f"zk_heev_dd_allpairs failed: {status_str(rc)}: {ctx.last_error()}")
@@ -358,6 +369,7 @@ def heev_mp(ctx: Context, mats, limbs: int = 8, opts: ZkOpts | None = None):
         keep += [w, vb, info]
         outs.append((w, vb.transpose(1, 2) if vb is not None else None, info, n))
     op = ctypes.byref(opts) if opts is not None else None
+    ctx._inputs_ready()
     rc = lib.zk_heev_mp(ctx.handle, count, H, O, op)
     if rc not in (ZK_OK, ZK_ENOCONV):
         raise RuntimeError(f"zk_heev_mp failed: {status_str(rc)}: {ctx.last_error()}")
@@ -498,6 +510,7 @@ def svd(ctx: Context, mats, opts: ZkOpts | None = None):
         keep += [s, ub, vb, info]
         outs.append((s, ub.transpose(1, 2) if want else None, vb.transpose(1, 2) if want else None, info, k))
     op = ctypes.byref(opts) if opts is not None else None
+    ctx._inputs_ready()
     rc = lib.zk_svd_dd(ctx.handle, count, A, O, op)
     if rc not in (ZK_OK, ZK_ENOCONV):
         raise RuntimeError(f"zk_svd_dd failed: {status_str(rc)}: {ctx.last_error()}")
@@ -543,7 +556,7 @@ def mps_two_site(ctx: Context, A, B, gate, chi_max: int, cutoff: float = 0.0, op
     so = [torch.zeros((chi_max,), dtype=torch.float64, device=dev) for _ in range(2)]
     P2 = ctypes.c_void_p * 2
     chi_out = ctypes.c_int(0)
-    torch.cuda.current_stream().synchronize()
+    ctx._inputs_ready()
     rc = lib.zk_mps_two_site_dd(ctx.handle, M // 2, chi, N // 2, P2(keep[0].data_ptr(), keep[1].data_ptr()),
                                 P2(keep[2].data_ptr(), keep[3].data_ptr()), P2(keep[4].data_ptr(), keep[5].data_ptr()),
                                 chi_max, float(cutoff), P2(Ao[0].data_ptr(), Ao[1].data_ptr()),
@@ -581,6 +594,7 @@ def heev_fp64(ctx: Context, mats):
         W[i], Vp[i], ld[i] = w.data_ptr(), vb.data_ptr(), n
         res.append((w, vb.transpose(0, 1)))
         keep += [w, vb]
+    ctx._inputs_ready()
     rc = lib.zk_heev_fp64(ctx.handle, count, H, W, Vp, ld)
     if rc != ZK_OK:
         raise RuntimeError(f"zk_heev_fp64 failed: {status_str(rc)}: {ctx.last_error()}")
@@ -599,6 +613,7 @@ def rqi_refine(ctx: Context, planes, w0: torch.Tensor, V0: torch.Tensor, limbs_o
     keep += [w0c, V0c]
     want = True if opts is None else bool(opts.want_vectors)
     o, w, V, info = _alloc_out(n, limbs_out, want, w0.device, keep, npairs=k)
+    ctx._inputs_ready()
     rc = lib.zk_rqi_refine(ctx.handle, limbs_out, ctypes.byref(h), k, ctypes.c_void_p(w0c.data_ptr()),
                            ctypes.c_void_p(V0c.data_ptr()), n, ctypes.byref(o),
                            ctypes.byref(opts) if opts is not None else None)
